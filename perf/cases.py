@@ -167,17 +167,19 @@ def _trajectories(c, n, gen):
 RECORD = ("worker", "target", "actions", "rewards", "dones")
 
 
-def _learner_side(c, x, lo, hi):
-    """The learner network's tensors for trajectories lo..hi-1, and outputs and workspace for one loss call."""
-    T, A, B = c["T"], c["A"], hi - lo
+def _learner_side(c, x, which):
+    """The learner network's tensors for the trajectories `which` (a slice, or a tensor of numbers), and outputs and
+    workspace for one loss call."""
+    T, A = c["T"], c["A"]
     W = A if c["dist"] == CATEGORICAL else 2 * A
-    learner, values = x["learner"][:, lo:hi], x["values"][:, lo:hi]
+    learner, values, bootstrap = x["learner"][:, which], x["values"][:, which], x["bootstrap"][which]
+    B = bootstrap.numel()
     if c["batch_major"]:
         learner, values = learner.transpose(0, 1), values.transpose(0, 1)
     learner = learner.to(torch.bfloat16) if c["learner_bf16"] else learner
     shape = (B, T, W) if c["batch_major"] else (T, B, W)
     # (the bootstrap values as a tensor of their own: a slice may start off the boundary that the library asks for)
-    return dict(learner=learner.contiguous(), values=values.contiguous(), bootstrap=x["bootstrap"][lo:hi].clone(),
+    return dict(learner=learner.contiguous(), values=values.contiguous(), bootstrap=bootstrap.clone(),
                 out=binding.alloc_loss_out(*shape, packed=c["packed"]),
                 workspace=torch.empty(binding.impact_loss_workspace_bytes(c["dist"], T, B, A), dtype=torch.uint8, device="cuda"))
 
@@ -204,7 +206,7 @@ def prepare(case, seed):
     s = dict(c=c, cfg=_hyper(c))
     if op == "batch":
         x = _trajectories(c, B, gen)
-        s.update(_learner_side(c, x, 0, B))
+        s.update(_learner_side(c, x, slice(0, B)))
         es = torch.bfloat16 if c["storage"] == "bf16" else torch.float32
         s["batch"] = {k: v.to(es) if v.dtype == torch.float32 else v for k, v in x.items() if k in RECORD}
     elif op == "insert":
@@ -217,7 +219,7 @@ def prepare(case, seed):
         cuts = list(range(0, n, c["fragment"])) + [n]
         s["fragments"] = [{k: x[k][:, i:j].contiguous() for k in RECORD if k != "target"} for i, j in zip(cuts, cuts[1:])]
         s["targets"] = [x["target"][:, b * B:(b + 1) * B].contiguous() for b in range(LOOP_BATCHES)]
-        s["steps"] = [_learner_side(c, x, b * B, (b + 1) * B) for _ in range(LOOP_K) for b in range(LOOP_BATCHES)]
+        s["steps"] = [_learner_side(c, x, slice(b * B, (b + 1) * B)) for _ in range(LOOP_K) for b in range(LOOP_BATCHES)]
         s["slots"] = [_pinned(B) for _ in s["steps"]]           # a set per step in flight: the kernels read them in place
         s["counts"] = _pinned(B)[1]
         s["ring"] = _ring(c, n, LOOP_K)
@@ -227,14 +229,12 @@ def prepare(case, seed):
         x = _trajectories(c, n, gen)
         s["ring"] = _ring(c, n, 1 << 30)
         binding.impact_buffer_insert(s["ring"], {k: x[k] for k in RECORD})
+        which = torch.arange(B, device="cuda") if c["slots"] == "ring" else torch.randperm(n, generator=gen, device="cuda")[:B]
+        s["dev_slots"] = which.to(torch.int32)
         if op == "step":
-            s.update(_learner_side(c, x, 0, B))
+            s.update(_learner_side(c, x, which))
         else:
             s["dst"] = binding.alloc_batch(s["ring"], B)
-        if c["slots"] == "scattered":
-            s["dev_slots"] = torch.randperm(n, generator=gen, device="cuda")[:B].to(torch.int32)
-        elif op == "gather":
-            s["dev_slots"] = torch.arange(B, dtype=torch.int32, device="cuda")
         s["slots"], s["counts"] = _pinned(B), _pinned(B)[1]
     return s
 
@@ -344,3 +344,101 @@ def tolerance(case):
     if c["op"] == "insert":
         return {"rel": 1e-14}
     return {"rel": 4e-7}
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# the same in 64 bits, by plain torch
+# ---------------------------------------------------------------------------------------------------------------
+
+def _stored(c, x):
+    """A float tensor as the ring keeps it."""
+    return (x.to(torch.bfloat16) if c["storage"] == "bf16" else x).double()
+
+
+def _logp64(c, dist, actions):
+    if c["dist"] == CATEGORICAL:
+        return torch.log_softmax(dist, dim=2).gather(2, actions.long().unsqueeze(2)).squeeze(2)
+    mean, ls = dist[..., :c["A"]], dist[..., c["A"]:]
+    return (-0.5 * (actions - mean) ** 2 * torch.exp(-2 * ls) - ls - 0.5 * math.log(2 * math.pi)).sum(dim=2)
+
+
+def _loss64(c, x, which):
+    """What one loss call on the trajectories `which` returns, from the definition of the loss."""
+    h, A = _hyper(c), c["A"]
+    learner = x["learner"][:, which]
+    z = (learner.to(torch.bfloat16) if c["learner_bf16"] else learner).double()
+    V, boot = x["values"][:, which].double(), x["bootstrap"][which].double()
+    worker, target, r = x["worker"][:, which], x["target"][:, which], _stored(c, x["rewards"][:, which])
+    done = x["dones"][:, which]
+    act = x["actions"][:, which]
+    act = act.long() if c["dist"] == CATEGORICAL else _stored(c, act)
+    zt = _stored(c, target)
+    if c["cached"]:                        # computed when the distributions arrive, from fp32
+        lw, lt = _logp64(c, worker.double(), act), _logp64(c, target.double(), act)
+    else:
+        lw, lt = _logp64(c, _stored(c, worker), act), _logp64(c, zt, act)
+    T, B = V.shape
+    w = torch.exp(lt - lw)
+    gamma = h.gamma * (1.0 - done.double())
+    delta = w.clamp(max=h.rho_bar) * (r + gamma * torch.cat([V[1:], boot[None]]) - V)
+    g = gamma * h.lam * w.clamp(max=h.c_bar)
+    adv, acc = torch.empty_like(V), torch.zeros_like(boot)
+    for t in range(T - 1, -1, -1):
+        acc = delta[t] + g[t] * acc
+        adv[t] = acc
+    R = torch.exp(_logp64(c, z, act) - torch.maximum(lt, lw - math.log(h.rho_clip)))
+    lo, hi = 1.0 - h.eps, 1.0 + h.eps
+    surrogate = torch.minimum(R * adv, R.clamp(lo, hi) * adv)
+    clipped = ((adv > 0) & (R > hi)) | ((adv < 0) & (R < lo))
+    M = T * B
+    gp = torch.where(clipped, torch.zeros_like(R), -adv * R / M).unsqueeze(2)      # dL / d log pi_theta(a)
+    ce, ck = h.ent_coeff / M, h.kl_coeff / M
+    if c["dist"] == CATEGORICAL:
+        lp, lq = torch.log_softmax(z, dim=2), torch.log_softmax(zt, dim=2)
+        p, q = lp.exp(), lq.exp()
+        H, KL = -(p * lp).sum(dim=2), (q * (lq - lp)).sum(dim=2)
+        taken = torch.zeros_like(p).scatter_(2, act.unsqueeze(2), 1.0)
+        grad = gp * (taken - p) + ce * p * (lp + H.unsqueeze(2)) + ck * (p - q)
+    else:
+        mu, ls, mt, lst = z[..., :A], z[..., A:], zt[..., :A], zt[..., A:]
+        inv = torch.exp(-2 * ls)
+        H = (ls + 0.5 * (1 + math.log(2 * math.pi))).sum(dim=2)
+        q = (torch.exp(2 * lst) + (mu - mt) ** 2) * inv
+        KL = (ls - lst + 0.5 * q - 0.5).sum(dim=2)
+        grad = torch.cat([gp * (act - mu) * inv + ck * (mu - mt) * inv,
+                          gp * ((act - mu) ** 2 * inv - 1) + ck * (1 - q) - ce], dim=2)
+    if c["cached"] and not c["kl"]:
+        KL = torch.zeros_like(KL)          # the target's distribution is not kept
+    pg, vf = -surrogate.mean(), 0.5 * (adv ** 2).mean()
+    total = pg + h.vf_coeff * vf - h.ent_coeff * H.mean() + h.kl_coeff * KL.mean()
+    gV = -h.vf_coeff * adv / M
+    lay = (lambda t: t.transpose(0, 1).contiguous()) if c["batch_major"] else (lambda t: t)
+    out = dict(grad_dist=lay(grad), loss5=torch.stack([total, pg, vf, H.mean(), KL.mean()]),
+               fractions=torch.stack([clipped.double().mean(), (w > h.rho_bar).double().mean()]))
+    if c["packed"]:
+        out["step_outputs"] = lay(torch.stack([gV, V + adv, adv, torch.zeros_like(adv)], dim=2))
+        return {k: out[k] for k in ("grad_dist", "step_outputs", "loss5", "fractions")}
+    out.update(grad_values=lay(gV), vs=lay(V + adv), adv=lay(adv))
+    return {k: out[k] for k in ("grad_dist", "grad_values", "vs", "adv", "loss5", "fractions")}
+
+
+def exact(case, seed):
+    c = dict(DEFAULTS, **case)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(int(seed))
+    B, op = c["B"], c["op"]
+    if op == "gather" or (op == "insert" and not c["cached"]):
+        return None                        # copies and roundings
+    if op == "insert":
+        x = _trajectories(c, B, gen)
+        act = x["actions"] if c["dist"] == CATEGORICAL else _stored(c, x["actions"])
+        pair = torch.stack([_logp64(c, x["worker"].double(), act), _logp64(c, x["target"].double(), act)], dim=2)
+        return {"before": None, "logp": pair.transpose(0, 1).contiguous().reshape(-1), "after": None}
+    if op == "loop":
+        x = _trajectories(c, LOOP_BATCHES * B, gen)
+        return [_loss64(c, x, slice(b * B, (b + 1) * B)) for _ in range(LOOP_K) for b in range(LOOP_BATCHES)]
+    if op == "batch" or c["slots"] == "ring":
+        return _loss64(c, _trajectories(c, B, gen), slice(0, B))
+    n = B + B // 2 + 1
+    x = _trajectories(c, n, gen)
+    return _loss64(c, x, torch.randperm(n, generator=gen, device="cuda")[:B])
