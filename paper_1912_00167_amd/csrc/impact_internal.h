@@ -81,6 +81,7 @@ struct ReduceArgs {
     float vf_coeff, ent_coeff, kl_coeff;
     float *loss5;
     float *fractions;
+    bool dpp;                 // see reduce_tiles
 };
 
 __host__ __device__ inline int num_tiles(int B) { return (B + NB - 1) / NB; }
@@ -100,6 +101,26 @@ bool launch_loss_cat_cached(int dtype, bool slot_major, LossArgs &a, hipStream_t
 bool launch_loss_cat_u8(int dtype, bool slot_major, LossArgs &a, hipStream_t s);
 bool launch_loss_gauss_cached(int dtype, bool slot_major, LossArgs &a, hipStream_t s);
 void launch_loss_generic(int dist, int dtype, bool slot_major, const LossArgs &a, hipStream_t s);
+
+// Shape of a launch of the register-resident kernels (loss_lanes.h): 2^p_log2 lanes per step, 2^nb_log2 trajectories
+// per workgroup, `rows` time steps per chunk, nchunk chunks; in the scan, 2^l_log2 lanes per trajectory with per_lane rows
+// each (per_lane_pad: up to a multiple of the scan's block); t_fastest: neighbouring lanes take neighbouring time steps
+// (else neighbouring trajectories).  rows_magic, per_lane_magic: i / rows = (i * rows_magic) >> 20 and
+// i / per_lane = (i * per_lane_magic) >> 16 for 0 <= i < 1024.  Strides: bytes between time steps
+// (_t) and between trajectories or slots (_b) of the buffer-side tensors; elements, in steps, of the learner's.
+constexpr int LANES_MAX_THREADS = 1024, LANES_MAX_NB = 64, LANES_MAX_ELEMS = 512;
+struct LanesShape {
+    int p_log2, nb_log2, rows, nchunk, l_log2, t_fastest, per_lane, per_lane_pad, rows_magic, per_lane_magic, waves;
+    unsigned dist_b, dist_t, act_b, act_t, lp_b, lp_t, rew_b, rew_t, done_b, done_t, ln_b, ln_t;
+};
+// False where there is no such kernel (more than LANES_MAX_ELEMS actions).  Sets a.num_partials.
+bool launch_loss_lanes(int dist, int dtype, bool slot_major, LossArgs &a, hipStream_t s);
+// One kernel of the family, by the element type of the buffer's floats: R elements per lane (1..6 or 8).
+struct LanesLaunch { unsigned blocks, threads, lds_bytes; int R; };
+void launch_lanes_cat_f32(const LanesLaunch &l, const LossArgs &a, const LanesShape &g, hipStream_t s);
+void launch_lanes_cat_bf16(const LanesLaunch &l, const LossArgs &a, const LanesShape &g, hipStream_t s);
+void launch_lanes_gauss_f32(const LanesLaunch &l, const LossArgs &a, const LanesShape &g, hipStream_t s);
+void launch_lanes_gauss_bf16(const LanesLaunch &l, const LossArgs &a, const LanesShape &g, hipStream_t s);
 void launch_reduce(const ReduceArgs &r, hipStream_t s);
 // A completion counter (zero between launches) for a loss call on this stream that has no buffer handle, or null
 // (stream_counters.hip): with one, the kernel's last workgroup sums the loss terms and no second launch follows.

@@ -113,6 +113,20 @@ __device__ __forceinline__ void set_priority_band(int band)
     }
 }
 
+// Read one word of each of the first seven 64-byte lines of the kernel's arguments (LossArgs and what follows it), all at
+// once: the compiler loads arguments where they are needed, and each line touched for the first time is a memory latency
+// of its own, one after the other.
+__device__ __forceinline__ void touch_arguments()
+{
+    static_assert(sizeof(LossArgs) > 256 && sizeof(LossArgs) + sizeof(LanesShape) > 384, "no line past the arguments is read");
+    unsigned w0, w1, w2, w3, w4, w5, w6;
+    asm volatile("s_load_dword %0, %7, 0x0\n\ts_load_dword %1, %7, 0x40\n\ts_load_dword %2, %7, 0x80\n\t"
+                 "s_load_dword %3, %7, 0xc0\n\ts_load_dword %4, %7, 0x100\n\ts_load_dword %5, %7, 0x140\n\t"
+                 "s_load_dword %6, %7, 0x180\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(w0), "=&s"(w1), "=&s"(w2), "=&s"(w3), "=&s"(w4), "=&s"(w5), "=&s"(w6)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+}
+
 // Workgroup -> tile map.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs;
 // give each XCD a contiguous range of tiles so that neighbouring tiles, which share
 // 128-byte lines of the [T][B] tensors, meet in the same L2.
@@ -431,6 +445,33 @@ __device__ __forceinline__ double wave_sum(double x)
     return x;
 }
 
+// ---- exchange between lanes by DPP: an operand of the instruction, where a shuffle is a trip through the LDS pipe ----
+
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_word(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false); }
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ float dpp(float x) { return __int_as_float(dpp_word<CTRL, ROWS>(__float_as_int(x))); }
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double dpp(double x)
+{
+    return __hiloint2double(dpp_word<CTRL, ROWS>(__double2hiint(x)), dpp_word<CTRL, ROWS>(__double2loint(x)));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;    // the last lane of a row of 16 to the next row; of two to the next two
+
+// Sum over the wavefront, in lane 63.
+template <typename T>
+__device__ __forceinline__ T wave_sum_63(T x)
+{
+    x += dpp<DPP_XOR1>(x);
+    x += dpp<DPP_XOR2>(x);
+    x += dpp<DPP_HALF_MIRROR>(x);
+    x += dpp<DPP_MIRROR>(x);                       // every lane of a row of 16 holds the row's sum
+    x += dpp<DPP_BCAST15, 0xA>(x);                 // (rows that receive nothing add zero)
+    x += dpp<DPP_BCAST31, 0xC>(x);
+    return x;
+}
+
 // U tiles per lane, from tile i0 on, 64 apart: all the loads first (one exposed memory latency), then the
 // additions in the order of the tiles.  GUARD: the block may reach past the last tile.
 template <int U, bool GUARD>
@@ -458,18 +499,20 @@ __device__ __forceinline__ void add_tile_block(const float *partials, int i0, in
 // the five loss terms into NaN.
 // The wavefront that runs this is the last one at work on the chip, so every memory latency here is
 // exposed: the loads go out in blocks as large as the registers hold.
-// Blocks of 16 tiles per lane (8 registers each); with tile groups a launch leaves a few hundred sets of sums,
-// one round of loads.
+// Blocks of U tiles per lane (8 registers each): 16 where the calling kernel has the registers (with tile groups a
+// launch leaves a few hundred sets of sums, one round of loads).  DPP: the lanes combine by DPP, which takes 0.4 us less
+// than shuffles, in another order.
+template <int U = 16, bool DPP = false>
 __device__ __forceinline__ void reduce_tiles(const float *partials, int num_tiles, double inv_M, float vf_coeff,
                                              float ent_coeff, float kl_coeff, float *loss5, float *fractions, int lane)
 {
     double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int done = 0;                                  // tiles before this one are summed
-    for (; num_tiles - done >= 64 * 16; done += 64 * 16) add_tile_block<16, false>(partials, done + lane, num_tiles, v);
-    for (; done < num_tiles; done += 64 * 8) add_tile_block<8, true>(partials, done + lane, num_tiles, v);
+    for (; num_tiles - done >= 64 * U; done += 64 * U) add_tile_block<U, false>(partials, done + lane, num_tiles, v);
+    for (; done < num_tiles; done += 64 * (U / 2)) add_tile_block<U / 2, true>(partials, done + lane, num_tiles, v);
 #pragma unroll
-    for (int j = 0; j < 7; ++j) v[j] = wave_sum(v[j]);
-    if (lane == 0) {
+    for (int j = 0; j < 7; ++j) v[j] = DPP ? wave_sum_63(v[j]) : wave_sum(v[j]);
+    if (lane == (DPP ? 63 : 0)) {
         if (fractions) {                           // counts of steps (exact in fp32 per tile, in fp64 here) over M
             fractions[0] = (float)(v[5] * inv_M);
             fractions[1] = (float)(v[6] * inv_M);

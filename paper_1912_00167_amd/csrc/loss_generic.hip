@@ -1,7 +1,8 @@
 // Shape-generic loss kernels: any number of actions / action dimension, any batch size,
 // no alignment requirement.  Same tiling and scan as the specialised kernels, but every
 // thread reads the values of its own step straight from global memory, in several passes.
-// Slower; used for shapes without a specialised kernel and for ragged batches.
+// For records too long for the register-resident kernels (more than LANES_MAX_ELEMS actions) and tensors too large for
+// their 32-bit strides.
 #include "loss_device.h"
 
 namespace impact {
@@ -219,14 +220,18 @@ void launch_loss_generic(int dist, int dtype, bool slot_major, const LossArgs &a
 
 // ---- final reduction of the per-workgroup partial sums as a launch of its own: one wavefront ----------
 
+template <bool DPP>
 __global__ __launch_bounds__(64) void reduce_partials(const ReduceArgs r)
 {
-    reduce_tiles(r.partials, r.num_tiles, r.inv_M, r.vf_coeff, r.ent_coeff, r.kl_coeff, r.loss5, r.fractions, threadIdx.x);
+    reduce_tiles<16, DPP>(r.partials, r.num_tiles, r.inv_M, r.vf_coeff, r.ent_coeff, r.kl_coeff, r.loss5, r.fractions, threadIdx.x);
 }
 
 void launch_reduce(const ReduceArgs &r, hipStream_t s)
 {
-    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(64), 0, s, r);
+    // (the order in which the lanes combine is that of the kernel that left the sums: the same bits with and without
+    // this launch)
+    if (r.dpp) hipLaunchKernelGGL((reduce_partials<true>), dim3(1), dim3(64), 0, s, r);
+    else hipLaunchKernelGGL((reduce_partials<false>), dim3(1), dim3(64), 0, s, r);
 }
 
 }  // namespace impact
