@@ -618,11 +618,9 @@ static impact_status_t run_loss(int dist, int dtype, const Planes *planes, int T
             launched = dist == IMPACT_CATEGORICAL ? launch_loss_cat_static(dtype, slot_major, a, s)
                                                   : launch_loss_gauss_static(dtype, slot_major, a, s);
     }
-    // any shape, up to 512 actions
-    const bool lanes = !launched && launch_loss_lanes(dist, dtype, slot_major, a, s);
-    if (!launched && !lanes) launch_loss_generic(dist, dtype, slot_major, a, s);
+    if (!launched) launch_loss_generic(dist, dtype, slot_major, a, s);
     if (!done_count) {
-        ReduceArgs r{a.partials, a.num_partials, 1.0 / M, cfg->vf_coeff, cfg->ent_coeff, cfg->kl_coeff, out->loss5, out->fractions, lanes};
+        ReduceArgs r{a.partials, a.num_partials, 1.0 / M, cfg->vf_coeff, cfg->ent_coeff, cfg->kl_coeff, out->loss5, out->fractions, a.dpp};
         launch_reduce(r, s);
     }
     return hipGetLastError() == hipSuccess ? IMPACT_OK : IMPACT_ERR_HIP;

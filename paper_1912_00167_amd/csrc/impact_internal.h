@@ -59,7 +59,8 @@ struct LossArgs {
     float *adv;               // [T][B] or null
     float4 *step_out;         // [T][B] records {dL/dV, vs, adv, 0} in place of the three tensors above, or null
     float *partials;          // [num_partials][PARTIAL_STRIDE]
-    int num_partials;         // sets of partial sums the launch leaves (one per workgroup); set by the launcher
+    mutable int num_partials; // sets of partial sums the launch leaves (one per workgroup); set by the launcher
+    mutable bool dpp;         // the order in which their last sum combines (see reduce_tiles); set by the launcher
     // Long trajectories of a small batch are cut into num_segs time segments of seg_chunks chunks each,
     // one workgroup per (tile, segment).  The scan is affine in its carry, acc_t = A_t + P_t * carry, so a
     // first launch (phase 1) only finds every segment's A and P at its first step (seg_agg[seg][b][2]) and a
@@ -100,6 +101,7 @@ bool launch_loss_cat_cached(int dtype, bool slot_major, LossArgs &a, hipStream_t
 // ... for one-byte action indices (a.act_bytes == 1), all three forms
 bool launch_loss_cat_u8(int dtype, bool slot_major, LossArgs &a, hipStream_t s);
 bool launch_loss_gauss_cached(int dtype, bool slot_major, LossArgs &a, hipStream_t s);
+// ... for any shape: the register-resident kernels below, or loss_generic where they do not reach
 void launch_loss_generic(int dist, int dtype, bool slot_major, const LossArgs &a, hipStream_t s);
 
 // Shape of a launch of the register-resident kernels (loss_lanes.h): 2^p_log2 lanes per step, 2^nb_log2 trajectories
@@ -113,8 +115,8 @@ struct LanesShape {
     int p_log2, nb_log2, rows, nchunk, l_log2, t_fastest, per_lane, per_lane_pad, rows_magic, per_lane_magic, waves;
     unsigned dist_b, dist_t, act_b, act_t, lp_b, lp_t, rew_b, rew_t, done_b, done_t, ln_b, ln_t;
 };
-// False where there is no such kernel (more than LANES_MAX_ELEMS actions).  Sets a.num_partials.
-bool launch_loss_lanes(int dist, int dtype, bool slot_major, LossArgs &a, hipStream_t s);
+// False where there is no such kernel (more than LANES_MAX_ELEMS actions).
+bool launch_loss_lanes(int dist, int dtype, bool slot_major, const LossArgs &a, hipStream_t s);
 // One kernel of the family, by the element type of the buffer's floats: R elements per lane (1..6 or 8).
 struct LanesLaunch { unsigned blocks, threads, lds_bytes; int R; };
 void launch_lanes_cat_f32(const LanesLaunch &l, const LossArgs &a, const LanesShape &g, hipStream_t s);

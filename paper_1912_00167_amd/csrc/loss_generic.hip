@@ -199,6 +199,7 @@ __global__ __launch_bounds__(NTHREADS) void loss_generic(const LossArgs a)
 
 void launch_loss_generic(int dist, int dtype, bool slot_major, const LossArgs &a, hipStream_t s)
 {
+    if (launch_loss_lanes(dist, dtype, slot_major, a, s)) return;
     const dim3 grid(num_tiles(a.B)), block(NTHREADS);
 #define IMPACT_LAUNCH(DIST, ST, LT, SLOT) hipLaunchKernelGGL((loss_generic<DIST, ST, LT, SLOT>), grid, block, 0, s, a)
 #define IMPACT_LAUNCH_LT(DIST, ST, SLOT)                              \

@@ -10,7 +10,7 @@ static int log2_of(int x)
     return l;
 }
 
-bool launch_loss_lanes(int dist, int dtype, bool slot_major, LossArgs &a, hipStream_t s)
+bool launch_loss_lanes(int dist, int dtype, bool slot_major, const LossArgs &a, hipStream_t s)
 {
     if (a.A > LANES_MAX_ELEMS) return false;
     const bool cat = dist == IMPACT_CATEGORICAL;
@@ -74,8 +74,8 @@ bool launch_loss_lanes(int dist, int dtype, bool slot_major, LossArgs &a, hipStr
     l.lds_bytes = (unsigned)((g.nchunk > 1 ? 4 : 2) * 64 * g.per_lane_pad * sizeof(double));
     l.R = (a.A + P - 1) / P;
     if (l.R == 7) l.R = 8;
-    a.num_segs = 1;
     a.num_partials = blocks;
+    a.dpp = true;
     if (cat) {
         if (dtype == IMPACT_F32) launch_lanes_cat_f32(l, a, g, s);
         else launch_lanes_cat_bf16(l, a, g, s);
