@@ -117,6 +117,8 @@ struct LanesShape {
 };
 // False where there is no such kernel (more than LANES_MAX_ELEMS actions).
 bool launch_loss_lanes(int dist, int dtype, bool slot_major, const LossArgs &a, hipStream_t s);
+// Whether they are the faster choice where a specialised kernel exists too.
+bool lanes_suit(int dist, int A, int T, int B, int chunk_rows);
 // One kernel of the family, by the element type of the buffer's floats: R elements per lane (1..6 or 8).
 struct LanesLaunch { unsigned blocks, threads, lds_bytes; int R; };
 void launch_lanes_cat_f32(const LanesLaunch &l, const LossArgs &a, const LanesShape &g, hipStream_t s);

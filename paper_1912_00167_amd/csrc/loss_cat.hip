@@ -8,10 +8,10 @@ bool launch_loss_cat_static(int dtype, bool slot_major, LossArgs &a, hipStream_t
 {
     if (a.act_bytes == 1) return launch_loss_cat_u8(dtype, slot_major, a, s);
     switch (a.A) {
-    case 4: launch_loss_static<CatPolicy<4, 1>>(dtype, slot_major, a, s); return true;
-    case 6: launch_loss_static<CatPolicy<6, 1>>(dtype, slot_major, a, s); return true;
-    case 9: launch_loss_static<CatPolicy<9, 1>>(dtype, slot_major, a, s); return true;
-    case 18: launch_loss_static<CatPolicy<18, 2>>(dtype, slot_major, a, s); return true;
+    case 4: return launch_loss_static<CatPolicy<4, 1>>(dtype, slot_major, a, s);
+    case 6: return launch_loss_static<CatPolicy<6, 1>>(dtype, slot_major, a, s);
+    case 9: return launch_loss_static<CatPolicy<9, 1>>(dtype, slot_major, a, s);
+    case 18: return launch_loss_static<CatPolicy<18, 2>>(dtype, slot_major, a, s);
     default: return false;
     }
 }

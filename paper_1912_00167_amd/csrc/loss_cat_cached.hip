@@ -7,10 +7,10 @@ template <int MODE>
 static bool launch_mode(int dtype, bool slot_major, LossArgs &a, hipStream_t s)
 {
     switch (a.A) {
-    case 4: launch_loss_static<CatPolicy<4, 1, MODE>>(dtype, slot_major, a, s); return true;
-    case 6: launch_loss_static<CatPolicy<6, 1, MODE>>(dtype, slot_major, a, s); return true;
-    case 9: launch_loss_static<CatPolicy<9, 1, MODE>>(dtype, slot_major, a, s); return true;
-    case 18: launch_loss_static<CatPolicy<18, 2, MODE>>(dtype, slot_major, a, s); return true;
+    case 4: return launch_loss_static<CatPolicy<4, 1, MODE>>(dtype, slot_major, a, s);
+    case 6: return launch_loss_static<CatPolicy<6, 1, MODE>>(dtype, slot_major, a, s);
+    case 9: return launch_loss_static<CatPolicy<9, 1, MODE>>(dtype, slot_major, a, s);
+    case 18: return launch_loss_static<CatPolicy<18, 2, MODE>>(dtype, slot_major, a, s);
     default: return false;
     }
 }

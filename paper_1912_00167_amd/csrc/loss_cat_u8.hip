@@ -8,10 +8,9 @@ namespace impact {
 bool launch_loss_cat_u8(int dtype, bool slot_major, LossArgs &a, hipStream_t s)
 {
     if (a.A != 18) return false;
-    if (!a.logp) launch_loss_static<CatPolicy<18, 2, POLICY_FULL, uint8_t>>(dtype, slot_major, a, s);
-    else if (a.target) launch_loss_static<CatPolicy<18, 2, POLICY_CACHED_TARGET, uint8_t>>(dtype, slot_major, a, s);
-    else launch_loss_static<CatPolicy<18, 2, POLICY_CACHED, uint8_t>>(dtype, slot_major, a, s);
-    return true;
+    if (!a.logp) return launch_loss_static<CatPolicy<18, 2, POLICY_FULL, uint8_t>>(dtype, slot_major, a, s);
+    if (a.target) return launch_loss_static<CatPolicy<18, 2, POLICY_CACHED_TARGET, uint8_t>>(dtype, slot_major, a, s);
+    return launch_loss_static<CatPolicy<18, 2, POLICY_CACHED, uint8_t>>(dtype, slot_major, a, s);
 }
 
 }  // namespace impact

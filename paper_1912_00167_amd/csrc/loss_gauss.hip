@@ -7,9 +7,9 @@ namespace impact {
 bool launch_loss_gauss_static(int dtype, bool slot_major, LossArgs &a, hipStream_t s)
 {
     switch (a.A) {
-    case 3: launch_loss_static<GaussPolicy<3, 1>>(dtype, slot_major, a, s); return true;
-    case 6: launch_loss_static<GaussPolicy<6, 1>>(dtype, slot_major, a, s); return true;
-    case 17: launch_loss_static<GaussPolicy<17, 2>>(dtype, slot_major, a, s); return true;
+    case 3: return launch_loss_static<GaussPolicy<3, 1>>(dtype, slot_major, a, s);
+    case 6: return launch_loss_static<GaussPolicy<6, 1>>(dtype, slot_major, a, s);
+    case 17: return launch_loss_static<GaussPolicy<17, 2>>(dtype, slot_major, a, s);
     default: return false;
     }
 }

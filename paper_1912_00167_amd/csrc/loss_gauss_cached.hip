@@ -7,9 +7,9 @@ template <int MODE>
 static bool launch_mode(int dtype, bool slot_major, LossArgs &a, hipStream_t s)
 {
     switch (a.A) {
-    case 3: launch_loss_static<GaussPolicy<3, 1, MODE>>(dtype, slot_major, a, s); return true;
-    case 6: launch_loss_static<GaussPolicy<6, 1, MODE>>(dtype, slot_major, a, s); return true;
-    case 17: launch_loss_static<GaussPolicy<17, 2, MODE>>(dtype, slot_major, a, s); return true;
+    case 3: return launch_loss_static<GaussPolicy<3, 1, MODE>>(dtype, slot_major, a, s);
+    case 6: return launch_loss_static<GaussPolicy<6, 1, MODE>>(dtype, slot_major, a, s);
+    case 17: return launch_loss_static<GaussPolicy<17, 2, MODE>>(dtype, slot_major, a, s);
     default: return false;
     }
 }

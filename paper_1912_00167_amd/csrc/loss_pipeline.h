@@ -567,15 +567,19 @@ void launch_loss_static_nw(int dtype, bool slot_major, LossArgs &a, hipStream_t 
     }
 }
 
+// False (nothing launched) where the register-resident kernels are the better choice.
 template <class Policy>
-void launch_loss_static(int dtype, bool slot_major, LossArgs &a, hipStream_t s)
+bool launch_loss_static(int dtype, bool slot_major, LossArgs &a, hipStream_t s)
 {
+    constexpr int CHUNK_ROWS = NWAVES * (64 / Policy::LANES / NB);
+    if (lanes_suit(Policy::ACT > 0 ? IMPACT_DIAG_GAUSSIAN : IMPACT_CATEGORICAL, a.A, a.T, a.B, CHUNK_ROWS)) return false;
     switch (waves_per_tile<Policy>(a, slot_major)) {
     case 1: launch_loss_static_nw<Policy, 1>(dtype, slot_major, a, s); break;
     case 2: launch_loss_static_nw<Policy, 2>(dtype, slot_major, a, s); break;
     case 3: launch_loss_static_nw<Policy, 3>(dtype, slot_major, a, s); break;
     default: launch_loss_static_nw<Policy, NWAVES>(dtype, slot_major, a, s); break;
     }
+    return true;
 }
 
 }  // namespace impact

@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import workloads
-from gpu_common import check_against_oracle, say, shape_workload, to_device
+from gpu_common import check_against_oracle, gpu_loss, say, shape_workload, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +80,21 @@ def test_masked_actions(env, mask):
     torch.cuda.synchronize()
     check_against_oracle(wl, x, {k: v.cpu().numpy() for k, v in out.items()}, label="masked")
     assert not out["grad_dist"][..., 5:].any()
+
+
+# on both sides of each line at which a specialised record changes from the pipeline to these kernels: the number of
+# trajectories, one chunk of the pipeline and more, short and long trajectories on few compute units
+ROUTES = [("categorical", 33, 1024, 18), ("categorical", 33, 1032, 18), ("categorical", 16, 40, 18), ("categorical", 17, 40, 18),
+          ("categorical", 32, 24, 6), ("categorical", 33, 24, 6), ("gaussian", 20, 192, 6), ("gaussian", 20, 200, 6), ("gaussian", 188, 12, 17),
+          ("gaussian", 189, 12, 17), ("categorical", 355, 40, 18), ("categorical", 356, 40, 18), ("categorical", 600, 192, 18)]
+
+
+@pytest.mark.parametrize("dist,T,Bn,A", ROUTES)
+def test_specialised_records(env, dist, T, Bn, A):
+    torch, binding = env
+    base = workloads.C2 if dist == "categorical" else workloads.C3
+    wl = shape_workload(replace(base, hyper=replace(base.hyper, kl_coeff=0.5)), T=T, B=Bn, A=A, storage="f32")
+    say(f"case lanes route {dist} T={T} B={Bn} A={A}")
+    x = workloads.make_batch(wl, stream=T + Bn)
+    got = gpu_loss(torch, binding, wl, x)
+    check_against_oracle(wl, x, got, label=f"{dist} T{T} B{Bn} A{A}")
