@@ -331,34 +331,23 @@ impact_status_t impact_buffer_reserve(impact_buffer_t *buf, int32_t n, int32_t *
     return IMPACT_OK;
 }
 
-// Enqueue the copies of one field for a list of slots, one launch per run of consecutive slots.
-static void scatter_field(PlaneKind kind, const void *src, void *dst, size_t slot_stride, int T, int n, int Wd,
-                          const int32_t *slots, hipStream_t s)
-{
-    int i = 0;
-    while (i < n) {
-        int j = i + 1;
-        while (j < n && slots[j] == slots[j - 1] + 1) ++j;
-        PlaneCopyArgs a{src, dst, T, n, Wd, i, slots[i], j - i, slot_stride};
-        launch_insert_plane(kind, a, s);
-        i = j;
-    }
-}
-
-// log pi(a) of one policy (which: 0 worker, 1 target) for the trajectories of a time-major fp32 tensor,
-// into the log-probability plane of the slots they went to; one launch per run of consecutive slots.
-static void cache_logp_field(impact_buffer *buf, int which, const float *dist_f32, int n, const int32_t *slots,
-                             hipStream_t s)
+// Enqueue the copies of all fields (a.task) for a list of slots, one launch per run of consecutive slots.
+static void scatter_fields(impact_buffer *buf, PlaneCopyArgs &a, int n, const int32_t *slots, hipStream_t s)
 {
     const impact_buffer_desc_t &d = buf->desc;
+    a.T = d.T;
+    a.n = n;
+    a.logp.dist = d.dist;
+    a.logp.A = d.A;
+    a.logp.act_bytes = buf->planes.act_bytes;
     int i = 0;
     while (i < n) {
         int j = i + 1;
         while (j < n && slots[j] == slots[j - 1] + 1) ++j;
-        LogpArgs a{dist_f32, buf->storage + buf->planes.actions, reinterpret_cast<double *>(buf->storage + buf->planes.logp),
-                   d.dist, d.storage, d.T, n, d.A, i, slots[i], j - i, which, buf->planes.stride_act,
-                   buf->planes.stride_lp, buf->planes.act_bytes};
-        launch_cache_logp(a, s);
+        a.i0 = i;
+        a.slot0 = slots[i];
+        a.cnt = j - i;
+        launch_insert_plane(d.storage == IMPACT_F32 ? PLANE_F32 : PLANE_BF16, a, s);
         i = j;
     }
 }
@@ -377,27 +366,24 @@ impact_status_t impact_buffer_insert(impact_buffer_t *buf, int32_t n, const impa
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const impact_buffer_desc_t &d = buf->desc;
-    const PlaneKind fk = d.storage == IMPACT_F32 ? PLANE_F32_TO_F32 : PLANE_F32_TO_BF16;
     char *base = buf->storage;
     (void)hipGetLastError();
     const Planes &pl = buf->planes;
-    const size_t es = (size_t)buf->es();           // strides below: in elements of the plane's type
-    if (pl.has_worker)
-        scatter_field(fk, src->worker_dist, base + pl.worker, pl.stride_dist / es, d.T, n, buf->W(), out_slots, s);
-    if (src->target_dist && pl.has_target)
-        scatter_field(fk, src->target_dist, base + pl.target, pl.stride_dist / es, d.T, n, buf->W(), out_slots, s);
+    PlaneCopyArgs a;
+    a.num = 0;
+    a.logp.actions = src->actions;
+    a.logp.stride_act = 0;
+    if (pl.has_worker) a.add(INSERT_FLOATS, src->worker_dist, base + pl.worker, pl.stride_dist, buf->W());
+    if (src->target_dist && pl.has_target) a.add(INSERT_FLOATS, src->target_dist, base + pl.target, pl.stride_dist, buf->W());
+    if (pl.has_logp) a.add(INSERT_LOGP, src->worker_dist, base + pl.logp, pl.stride_lp, buf->W(), 0);
+    if (pl.has_logp && src->target_dist) a.add(INSERT_LOGP, src->target_dist, base + pl.logp, pl.stride_lp, buf->W(), 1);
     if (d.dist == IMPACT_CATEGORICAL)
-        scatter_field(pl.act_bytes == 1 ? PLANE_U8 : PLANE_I32, src->actions, base + pl.actions,
-                      pl.stride_act / (size_t)pl.act_bytes, d.T, n, 1, out_slots, s);
+        a.add(pl.act_bytes == 1 ? INSERT_U8 : INSERT_I32, src->actions, base + pl.actions, pl.stride_act, 1);
     else
-        scatter_field(fk, src->actions, base + pl.actions, pl.stride_act / es, d.T, n, d.A, out_slots, s);
-    if (pl.has_logp) {
-        // after the actions: the log-probabilities are those of the action as stored
-        cache_logp_field(buf, 0, static_cast<const float *>(src->worker_dist), n, out_slots, s);
-        if (src->target_dist) cache_logp_field(buf, 1, static_cast<const float *>(src->target_dist), n, out_slots, s);
-    }
-    scatter_field(fk, src->rewards, base + pl.rewards, pl.stride_rew / es, d.T, n, 1, out_slots, s);
-    scatter_field(PLANE_U8, src->dones, base + pl.dones, pl.stride_done, d.T, n, 1, out_slots, s);
+        a.add(INSERT_FLOATS, src->actions, base + pl.actions, pl.stride_act, d.A);
+    a.add(INSERT_FLOATS, src->rewards, base + pl.rewards, pl.stride_rew, 1);
+    a.add(INSERT_U8, src->dones, base + pl.dones, pl.stride_done, 1);
+    scatter_fields(buf, a, n, out_slots, s);
     if (hipGetLastError() != hipSuccess) {
         // undo the bookkeeping: the slots just reserved become empty again
         for (int32_t i = 0; i < n; ++i) buf->count[out_slots[i]] = impact_buffer::kEmpty;
@@ -418,13 +404,15 @@ impact_status_t impact_buffer_put_target(impact_buffer_t *buf, int32_t n, const 
     for (int32_t i = 0; i < n; ++i)
         if (slots[i] < 0 || slots[i] >= buf->desc.num_slots) return IMPACT_ERR_INVALID_ARG;
     std::lock_guard<std::mutex> g(buf->mu);
-    const impact_buffer_desc_t &d = buf->desc;
-    const PlaneKind fk = d.storage == IMPACT_F32 ? PLANE_F32_TO_F32 : PLANE_F32_TO_BF16;
+    const Planes &pl = buf->planes;
     (void)hipGetLastError();
-    if (buf->planes.has_target)
-        scatter_field(fk, target_dist, buf->storage + buf->planes.target, buf->planes.stride_dist / (size_t)buf->es(),
-                      d.T, n, buf->W(), slots, static_cast<hipStream_t>(stream));
-    if (buf->planes.has_logp) cache_logp_field(buf, 1, target_dist, n, slots, static_cast<hipStream_t>(stream));
+    PlaneCopyArgs a;
+    a.num = 0;
+    a.logp.actions = buf->storage + pl.actions;
+    a.logp.stride_act = pl.stride_act;
+    if (pl.has_target) a.add(INSERT_FLOATS, target_dist, buf->storage + pl.target, pl.stride_dist, buf->W());
+    if (pl.has_logp) a.add(INSERT_LOGP, target_dist, buf->storage + pl.logp, pl.stride_lp, buf->W(), 1);
+    scatter_fields(buf, a, n, slots, static_cast<hipStream_t>(stream));
     if (hipGetLastError() != hipSuccess) return IMPACT_ERR_HIP;
     for (int32_t i = 0; i < n; ++i) buf->has_target[slots[i]] = 1;
     return IMPACT_OK;

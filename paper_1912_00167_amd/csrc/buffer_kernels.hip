@@ -17,107 +17,231 @@ __device__ __forceinline__ D convert(S x) { return (D)x; }
 template <>
 __device__ __forceinline__ bf16_t convert<float, bf16_t>(float x) { return to_bf16(x); }
 
-// dst[(slot0 + s)][t][k] = src[t][i0 + s][k] for s < cnt.  One thread per destination element,
-// so stores are contiguous; loads are contiguous runs of Wd elements.
-template <typename S, typename D>
-__global__ __launch_bounds__(256) void insert_plane(const PlaneCopyArgs a)
-{
-    const size_t per_slot = (size_t)a.T * a.Wd;
-    const size_t total = per_slot * a.cnt;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-        const int s = (int)(e / per_slot);
-        const size_t rem = e - (size_t)s * per_slot;
-        const int t = (int)(rem / a.Wd), k = (int)(rem - (size_t)t * a.Wd);
-        const S v = ((const S *)a.src)[((size_t)t * a.n + a.i0 + s) * a.Wd + k];
-        ((D *)a.dst)[(size_t)(a.slot0 + s) * a.slot_stride + rem] = convert<S, D>(v);
-    }
-}
+// ---- into the ring: dst[slot0 + s][t][.] = src[t][i0 + s][.] for s < cnt, all fields in one launch ----------
+//
+// Every workgroup takes one tile of one field.  A field's records lie one after the other along the trajectories in the
+// source and along the time steps in the ring, so a tile is a transpose through LDS, read and written in whole segments.
+// What bounds it: memory for large batches (see launch_insert_plane), the launch for small ones.
 
-// The same copy for records of 16 bytes and more, as a transpose through LDS: a workgroup takes a tile
-// of INSERT_NB trajectories x RT rows.  In: each wavefront reads whole rows of the source (the tile's
-// INSERT_NB records of a time step lie one after the other).  Out: each wavefront writes whole
-// trajectories' pieces (RT records, contiguous in the plane), converted, 16 bytes per lane.
-constexpr int INSERT_NB = 8;
+constexpr int INSERT_NB = 8;                       // trajectories per tile of records
 constexpr int INSERT_TILE_BYTES = 32768;
+constexpr int INSERT_SCALAR_NB = 64, INSERT_SCALAR_ROWS = 32;     // tile of a field with one element per step
 
 template <typename S, typename D>
-__global__ __launch_bounds__(256) void insert_tiles(const PlaneCopyArgs a, int RT)
+__device__ __forceinline__ void insert_records(const PlaneCopyArgs &a, const PlaneTask &k, int block, S *tile)
 {
-    __shared__ __align__(16) S tile[INSERT_TILE_BYTES / sizeof(S)];
     constexpr int VW = 16 / (int)sizeof(D);        // destination elements per 16-byte vector
+    constexpr int SV = 16 / (int)sizeof(S);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int s0 = blockIdx.x * INSERT_NB, t0 = blockIdx.y * RT;
-    const int nb = min(INSERT_NB, a.cnt - s0), rows = min(RT, a.T - t0);
-    const int row_elems = nb * a.Wd;               // of the tile, in the source
-    const int row_pitch = INSERT_NB * a.Wd;        // in LDS
+    const int across = (a.cnt + INSERT_NB - 1) / INSERT_NB;
+    const int ty = block / across, s0 = (block - ty * across) * INSERT_NB, t0 = ty * k.rows;
+    const int nb = min(INSERT_NB, a.cnt - s0), rows = min(k.rows, a.T - t0);
+    const int row_elems = nb * k.Wd;               // of the tile, in the source
+    const int row_pitch = INSERT_NB * k.Wd;        // in LDS
+    const S *src0 = (const S *)k.src + ((size_t)t0 * a.n + a.i0 + s0) * k.Wd;
+    const size_t src_pitch = (size_t)a.n * k.Wd;
     // several loads in flight per thread before the first LDS store (the loop bounds are run-time values,
     // which would otherwise leave one load latency exposed per element)
-    constexpr int U = 8;
-    const S *src0 = (const S *)a.src + ((size_t)t0 * a.n + a.i0 + s0) * a.Wd;
-    const size_t src_pitch = (size_t)a.n * a.Wd;
-    const int total = rows * row_elems;
-    const float inv_row = 1.0f / (float)row_elems;
-    for (int f0 = tid; f0 < total; f0 += 256 * U) {
-        S v[U];
-        int at[U];
+    if (row_elems % SV == 0 && (size_t)src0 % 16 == 0 && src_pitch % SV == 0) {
+        constexpr int U = 4;
+        const int row_vecs = row_elems / SV, total = rows * row_vecs;
+        const float inv_row = 1.0f / (float)row_vecs;
+        for (int f0 = tid; f0 < total; f0 += 256 * U) {
+            uint4 v[U];
+            int at[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int f = f0 + 256 * u;
-            const int r = (int)(((float)f + 0.5f) * inv_row), i = f - r * row_elems;
-            at[u] = r * row_pitch + i;
-            v[u] = f < total ? src0[(size_t)r * src_pitch + i] : S(0);
+            for (int u = 0; u < U; ++u) {
+                const int f = min(f0 + 256 * u, total - 1);
+                const int r = (int)(((float)f + 0.5f) * inv_row), i = (f - r * row_vecs) * SV;
+                at[u] = r * row_pitch + i;
+                v[u] = *(const uint4 *)(src0 + (size_t)r * src_pitch + i);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) *(uint4 *)(tile + at[u]) = v[u];       // (past the end: the last vector again)
         }
+    } else {
+        constexpr int U = 8;
+        const int total = rows * row_elems;
+        const float inv_row = 1.0f / (float)row_elems;
+        for (int f0 = tid; f0 < total; f0 += 256 * U) {
+            S v[U];
+            int at[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (f0 + 256 * u < total) tile[at[u]] = v[u];
+            for (int u = 0; u < U; ++u) {
+                const int f = min(f0 + 256 * u, total - 1);
+                const int r = (int)(((float)f + 0.5f) * inv_row), i = f - r * row_elems;
+                at[u] = r * row_pitch + i;
+                v[u] = src0[(size_t)r * src_pitch + i];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) tile[at[u]] = v[u];
+        }
     }
     __syncthreads();
-    const int piece = rows * a.Wd;                 // destination elements per trajectory
-    const float inv_wd = 1.0f / (float)a.Wd;
-    auto from_tile = [&](int j, int e) {           // element e of trajectory j's piece (e < 8192: exact in float)
-        const int r = (int)(((float)e + 0.5f) * inv_wd), k = e - r * a.Wd;
-        return convert<S, D>(tile[r * row_pitch + j * a.Wd + k]);
-    };
+    const int piece = rows * k.Wd;                 // destination elements per trajectory
+    const float inv_wd = 1.0f / (float)k.Wd;
     for (int j = wave; j < nb; j += 4) {
-        D *dst = (D *)a.dst + (size_t)(a.slot0 + s0 + j) * a.slot_stride + (size_t)t0 * a.Wd;
+        D *dst = (D *)((char *)k.dst + (size_t)(a.slot0 + s0 + j) * k.slot_stride) + (size_t)t0 * k.Wd;
         const int nvec = (((size_t)dst % 16) == 0) ? piece / VW : 0;
         for (int v = lane; v < nvec; v += 64) {
+            // element e of the trajectory's piece (below 8192: exact in float) is element c of row r
+            const int e = v * VW, r = (int)(((float)e + 0.5f) * inv_wd);
+            int c = e - r * k.Wd;
+            const S *from = tile + r * row_pitch + j * k.Wd;
             D w[VW];
 #pragma unroll
-            for (int q = 0; q < VW; ++q) w[q] = from_tile(j, v * VW + q);
+            for (int q = 0; q < VW; ++q) {
+                w[q] = convert<S, D>(from[c]);
+                if (++c == k.Wd) { c = 0; from += row_pitch; }
+            }
             ((uint4 *)dst)[v] = *(const uint4 *)w;
         }
-        for (int e = nvec * VW + lane; e < piece; e += 64) dst[e] = from_tile(j, e);
+        for (int e = nvec * VW + lane; e < piece; e += 64) {
+            const int r = (int)(((float)e + 0.5f) * inv_wd);
+            dst[e] = convert<S, D>(tile[r * row_pitch + j * k.Wd + e - r * k.Wd]);
+        }
     }
 }
 
+// One element per step: 64 trajectories x 32 steps, read along the trajectories, written along the steps.
 template <typename S, typename D>
-static bool launch_insert_tiles(const PlaneCopyArgs &a, hipStream_t s)
+__device__ __forceinline__ void insert_scalars(const PlaneCopyArgs &a, const PlaneTask &k, int block, S *tile)
 {
-    const size_t rec = (size_t)a.Wd * sizeof(S);              // bytes of one source record
-    if (rec < 16 || a.cnt < INSERT_NB || a.T > 65535 * 8) return false;
-    int RT = (int)(INSERT_TILE_BYTES / (INSERT_NB * rec)) & ~7;   // whole 16-byte vectors per piece, whatever Wd
-    if (RT < 8) return false;
-    RT = min(RT, (a.T + 7) & ~7);
-    const dim3 grid((a.cnt + INSERT_NB - 1) / INSERT_NB, (a.T + RT - 1) / RT);
-    if (grid.y > 65535) return false;
-    hipLaunchKernelGGL((insert_tiles<S, D>), grid, dim3(256), 0, s, a, RT);
-    return true;
+    constexpr int NB_ = INSERT_SCALAR_NB, ROWS = INSERT_SCALAR_ROWS, PITCH = NB_ + 1, U = NB_ * ROWS / 256;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int across = (a.cnt + NB_ - 1) / NB_;
+    const int ty = block / across, s0 = (block - ty * across) * NB_, t0 = ty * ROWS;
+    const int nb = min(NB_, a.cnt - s0), rows = min(ROWS, a.T - t0);
+    const S *src0 = (const S *)k.src + (size_t)t0 * a.n + a.i0 + s0;
+    S v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = src0[(size_t)min(wave + 4 * u, rows - 1) * a.n + min(lane, nb - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) tile[(wave + 4 * u) * PITCH + lane] = v[u];
+    __syncthreads();
+    const int t = tid & (ROWS - 1), j0 = tid / ROWS;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int j = j0 + u * (256 / ROWS);
+        if (t < rows && j < nb) ((D *)((char *)k.dst + (size_t)(a.slot0 + s0 + j) * k.slot_stride))[t0 + t] = convert<S, D>(tile[t * PITCH + j]);
+    }
 }
 
-void launch_insert_plane(PlaneKind kind, const PlaneCopyArgs &a, hipStream_t s)
+// One element per thread, for records too long for the tile (thousands of actions).
+template <typename S, typename D>
+__device__ __forceinline__ void insert_elements(const PlaneCopyArgs &a, const PlaneTask &k, int block, int blocks)
 {
-    const size_t total = (size_t)a.T * a.Wd * a.cnt;
-    if (total == 0) return;
-    if (kind == PLANE_F32_TO_F32 && launch_insert_tiles<float, float>(a, s)) return;
-    if (kind == PLANE_F32_TO_BF16 && launch_insert_tiles<float, bf16_t>(a, s)) return;
-    const unsigned blocks = (unsigned)min((size_t)65536, (total + 255) / 256);
-    switch (kind) {
-    case PLANE_F32_TO_F32: hipLaunchKernelGGL((insert_plane<float, float>), dim3(blocks), dim3(256), 0, s, a); break;
-    case PLANE_F32_TO_BF16: hipLaunchKernelGGL((insert_plane<float, bf16_t>), dim3(blocks), dim3(256), 0, s, a); break;
-    case PLANE_I32: hipLaunchKernelGGL((insert_plane<int32_t, int32_t>), dim3(blocks), dim3(256), 0, s, a); break;
-    case PLANE_U8: hipLaunchKernelGGL((insert_plane<uint8_t, uint8_t>), dim3(blocks), dim3(256), 0, s, a); break;
+    const size_t per_slot = (size_t)a.T * k.Wd, total = per_slot * a.cnt;
+    for (size_t e = (size_t)block * 256 + threadIdx.x; e < total; e += (size_t)blocks * 256) {
+        const int s = (int)(e / per_slot);
+        const size_t rem = e - (size_t)s * per_slot;
+        const int t = (int)(rem / k.Wd), c = (int)(rem - (size_t)t * k.Wd);
+        ((D *)((char *)k.dst + (size_t)(a.slot0 + s) * k.slot_stride))[rem] = convert<S, D>(((const S *)k.src)[((size_t)t * a.n + a.i0 + s) * k.Wd + c]);
     }
+}
+
+// log pi(a) of the action as the ring stores it, in fp64 with the library's exp and log, four lanes per step: this runs
+// once per trajectory, and is a chain of exponentials long (with one lane per step, 6.6 us for 128 trajectories of 50 steps,
+// A = 18, which was the longest launch of that insert).
+template <typename ST>
+__device__ __forceinline__ void insert_logp(const PlaneCopyArgs &a, const PlaneTask &k, int block)
+{
+    const LogpArgs &l = a.logp;
+    const size_t total = (size_t)a.cnt * a.T;
+    const int part = threadIdx.x & 3;
+    const size_t e = min((size_t)block * 64 + (threadIdx.x >> 2), total - 1);
+    // neighbouring steps are neighbouring trajectories of one time step: their records lie one after the other
+    const int t = (int)(e / a.cnt), s = (int)(e - (size_t)t * a.cnt);
+    const size_t from = (size_t)t * a.n + a.i0 + s;
+    const float *z = (const float *)k.src + from * k.Wd;
+    const size_t act_at = l.stride_act ? (size_t)t : from;
+    const char *actions = (const char *)l.actions + (l.stride_act ? (size_t)(a.slot0 + s) * l.stride_act : 0);
+    double lp;
+    if (l.dist == IMPACT_CATEGORICAL) {
+        const int given = l.act_bytes == 1 ? (int)((const uint8_t *)actions)[act_at] : ((const int *)actions)[act_at];
+        const int act = min(max(given, 0), l.A - 1);         // (the loss flags an index out of range)
+        float m = z[0];
+        for (int c = part; c < l.A; c += 4) m = fmaxf(m, z[c]);
+        m = fmaxf(m, dpp<DPP_XOR1>(m));
+        m = fmaxf(m, dpp<DPP_XOR2>(m));
+        double S = 0.0;
+        for (int c = part; c < l.A; c += 4) S += exp((double)z[c] - (double)m);
+        S += dpp<DPP_XOR1>(S);
+        S += dpp<DPP_XOR2>(S);
+        lp = ((double)z[act] - (double)m) - log(S);
+    } else {
+        lp = 0.0;
+        for (int d = part; d < l.A; d += 4) {
+            const double ls = (double)z[l.A + d];
+            const double x = l.stride_act ? (double)widen(((const ST *)actions)[act_at * l.A + d])
+                                          : (double)widen(convert<float, ST>(((const float *)actions)[act_at * l.A + d]));
+            const double diff = x - (double)z[d];
+            lp += -0.5 * diff * diff * exp(-2.0 * ls) - ls;
+        }
+        lp += dpp<DPP_XOR1>(lp);
+        lp += dpp<DPP_XOR2>(lp);
+        lp -= l.A * (double)kHalfLog2Pi;
+    }
+    if (part == 0) ((double *)((char *)k.dst + (size_t)(a.slot0 + s) * k.slot_stride))[2 * t + k.which] = lp;
+}
+
+template <typename ST>
+__global__ __launch_bounds__(256) void insert_fields(const PlaneCopyArgs a)
+{
+    extern __shared__ __align__(16) unsigned char insert_tile[];
+    int i = 0, first = 0;
+    while (i < a.num - 1 && (int)blockIdx.x >= a.task[i].end) first = a.task[i++].end;
+    const PlaneTask &k = a.task[i];
+    const int block = (int)blockIdx.x - first;
+    if (k.kind == INSERT_LOGP) insert_logp<ST>(a, k, block);
+    else if (k.kind == INSERT_I32) insert_scalars<int32_t, int32_t>(a, k, block, (int32_t *)insert_tile);
+    else if (k.kind == INSERT_U8) insert_scalars<uint8_t, uint8_t>(a, k, block, (uint8_t *)insert_tile);
+    else if (k.Wd == 1) insert_scalars<float, ST>(a, k, block, (float *)insert_tile);
+    else if (k.rows > 0) insert_records<float, ST>(a, k, block, (float *)insert_tile);
+    else insert_elements<float, ST>(a, k, block, k.end - first);
+}
+
+// 4096 trajectories of 128 steps (D = 17, bf16 ring), 271 MB: 60 us, 4.5 TB/s; field by field 28 + 28 + 15 + 6 + 4 us in
+// five launches, 88 us per call.
+void launch_insert_plane(PlaneKind kind, const PlaneCopyArgs &given, hipStream_t s)
+{
+    PlaneCopyArgs a = given;
+    const size_t steps = (size_t)a.T * a.cnt;
+    if (steps == 0 || a.num == 0) return;
+    size_t end = 0, lds = 0;
+    for (int i = 0; i < a.num; ++i) {
+        PlaneTask &k = a.task[i];
+        const size_t across = (a.cnt + INSERT_NB - 1) / INSERT_NB;
+        size_t blocks;
+        k.rows = 0;
+        if (k.kind == INSERT_LOGP) {
+            blocks = (steps + 63) / 64;
+        } else if (k.Wd == 1) {
+            blocks = ((size_t)(a.cnt + INSERT_SCALAR_NB - 1) / INSERT_SCALAR_NB) * ((a.T + INSERT_SCALAR_ROWS - 1) / INSERT_SCALAR_ROWS);
+            lds = max(lds, (size_t)INSERT_SCALAR_ROWS * (INSERT_SCALAR_NB + 1) * 4);
+        } else {
+            // rows per tile: a multiple of 8 (whole 16-byte vectors per trajectory's piece, whatever the record), as many
+            // as the tile holds, or down to half as many if they divide the trajectories better
+            const int most = (int)(INSERT_TILE_BYTES / ((size_t)INSERT_NB * k.Wd * 4));
+            if (most >= 1) {
+                k.rows = min(most, a.T);
+                if (most >= 8) {
+                    k.rows = min(most & ~7, (a.T + 7) & ~7);
+                    for (int r = k.rows; r >= 8 && 2 * r >= k.rows; r -= 8)
+                        if ((a.T + r - 1) / r * r < (a.T + k.rows - 1) / k.rows * k.rows) k.rows = r;
+                }
+                blocks = across * ((a.T + k.rows - 1) / k.rows);
+                lds = max(lds, (size_t)INSERT_NB * k.rows * k.Wd * 4);
+            } else {
+                blocks = min((size_t)65536, (steps * k.Wd + 255) / 256);
+            }
+        }
+        end += blocks;
+        k.end = (int)end;
+    }
+    const dim3 grid((unsigned)end), block(256);
+    if (kind == PLANE_F32) hipLaunchKernelGGL((insert_fields<float>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((insert_fields<bf16_t>), grid, block, lds, s, a);
 }
 
 // dst[t][b][.] = plane[slots[b]][t][.]: a byte copy, done in words of WB bytes (the largest of 4, 2, 1
@@ -233,52 +357,6 @@ void launch_gather_plane(const GatherArgs &a, hipStream_t s)
     case 2: hipLaunchKernelGGL((gather_tiles<uint16_t>), grid, block, 0, s, a, wpr, RT, slot_words); break;
     default: hipLaunchKernelGGL((gather_tiles<uint8_t>), grid, block, 0, s, a, wpr, RT, slot_words); break;
     }
-}
-
-// One thread per stored step: fp64 with the library's exp and log (this runs once per trajectory, when
-// it enters the buffer or when the target network's outputs are appended).
-template <int DIST, typename ST>
-__global__ __launch_bounds__(256) void cache_logp(const LogpArgs a)
-{
-    const int W = DIST == IMPACT_CATEGORICAL ? a.A : 2 * a.A;
-    const size_t total = (size_t)a.cnt * a.T;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-        // neighbouring threads take neighbouring trajectories of one time step: their records lie one
-        // after the other in the source tensor, which is where most of the bytes are
-        const int t = (int)(e / a.cnt), s = (int)(e - (size_t)t * a.cnt);
-        const float *z = a.dist_f32 + ((size_t)t * a.n + a.i0 + s) * W;
-        const char *act_slot = (const char *)a.actions_plane + (size_t)(a.slot0 + s) * a.stride_act;
-        double lp;
-        if (DIST == IMPACT_CATEGORICAL) {
-            const int stored = a.act_bytes == 1 ? (int)((const uint8_t *)act_slot)[t] : ((const int *)act_slot)[t];
-            const int act = min(max(stored, 0), a.A - 1);   // (the loss flags an index out of range)
-            float m = z[0];
-            for (int k = 1; k < a.A; ++k) m = fmaxf(m, z[k]);
-            double S = 0.0;
-            for (int k = 0; k < a.A; ++k) S += exp((double)z[k] - (double)m);
-            lp = ((double)z[act] - (double)m) - log(S);
-        } else {
-            const ST *act = (const ST *)act_slot + (size_t)t * a.A;
-            lp = -a.A * (double)kHalfLog2Pi;
-            for (int d = 0; d < a.A; ++d) {
-                const double ls = (double)z[a.A + d];
-                const double diff = (double)widen(act[d]) - (double)z[d];
-                lp += -0.5 * diff * diff * exp(-2.0 * ls) - ls;
-            }
-        }
-        double *slot_lp = (double *)((char *)a.logp_plane + (size_t)(a.slot0 + s) * a.stride_lp);
-        slot_lp[2 * t + a.which] = lp;
-    }
-}
-
-void launch_cache_logp(const LogpArgs &a, hipStream_t s)
-{
-    const size_t total = (size_t)a.cnt * a.T;
-    if (total == 0) return;
-    const dim3 grid((unsigned)min((size_t)65536, (total + 255) / 256)), block(256);
-    if (a.dist == IMPACT_CATEGORICAL) hipLaunchKernelGGL((cache_logp<IMPACT_CATEGORICAL, float>), grid, block, 0, s, a);
-    else if (a.storage == IMPACT_F32) hipLaunchKernelGGL((cache_logp<IMPACT_DIAG_GAUSSIAN, float>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((cache_logp<IMPACT_DIAG_GAUSSIAN, bf16_t>), grid, block, 0, s, a);
 }
 
 __global__ void zero_words(unsigned *p, int n)

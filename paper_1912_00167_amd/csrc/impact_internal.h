@@ -132,15 +132,36 @@ unsigned *done_counter_of_stream(hipStream_t s);
 void launch_zero_words(unsigned *p, int n, hipStream_t s);
 
 // Buffer data movement.  A "run" is cnt consecutive slots starting at slot0 that take
-// trajectories i0 .. i0+cnt-1 of a time-major source with n trajectories.
-struct PlaneCopyArgs {
+// trajectories i0 .. i0+cnt-1 of time-major sources with n trajectories.  One launch moves all fields of a run.
+struct PlaneTask {
     const void *src;     // time-major [T][n][Wd]
-    void *dst;           // slot-major [N][T][Wd], slots slot_stride elements apart (>= T * Wd)
-    int T, n, Wd;
-    int i0, slot0, cnt;
+    void *dst;           // slot-major plane [N][T][Wd], slots slot_stride bytes apart; log-probabilities: [N][T][2]
     size_t slot_stride;
+    int Wd;              // elements per record; log-probabilities: of the distribution
+    int kind;            // InsertKind
+    int which;           // log-probabilities: column of the plane
+    int rows;            // time steps per tile; the tiles of a task are numbered along the trajectories first
+    int end;             // first workgroup after this task's
 };
-enum PlaneKind { PLANE_F32_TO_F32, PLANE_F32_TO_BF16, PLANE_I32, PLANE_U8 };
+enum InsertKind { INSERT_FLOATS, INSERT_I32, INSERT_U8, INSERT_LOGP };
+constexpr int INSERT_TASKS = 8;
+// For the log-probabilities: the actions, which count as the ring stores them.
+struct LogpArgs {
+    const void *actions;         // time-major, about to be stored, or the ring's plane
+    size_t stride_act;           // bytes between slots of the plane; 0: time-major
+    int dist, A, act_bytes;      // act_bytes: categorical, of an index
+};
+struct PlaneCopyArgs {
+    int T, n, i0, slot0, cnt;
+    int num;
+    PlaneTask task[INSERT_TASKS];
+    LogpArgs logp;
+    void add(int kind, const void *src, void *dst, size_t slot_stride, int Wd, int which = 0)
+    {
+        task[num++] = PlaneTask{src, dst, slot_stride, Wd, kind, which, 0, 0};
+    }
+};
+enum PlaneKind { PLANE_F32, PLANE_BF16 };                  // what the ring stores the float fields as
 void launch_insert_plane(PlaneKind kind, const PlaneCopyArgs &a, hipStream_t s);
 
 struct GatherArgs {
@@ -152,18 +173,5 @@ struct GatherArgs {
     size_t slot_stride;
 };
 void launch_gather_plane(const GatherArgs &a, hipStream_t s);
-
-// log pi(a) of the trajectories i0 .. i0+cnt-1 of a time-major fp32 distribution tensor [T][n][W], for the
-// actions already stored in slots slot0 .. slot0+cnt-1, into column `which` of the plane logp[slot][T][2].
-struct LogpArgs {
-    const float *dist_f32;
-    const void *actions_plane;
-    double *logp_plane;
-    int dist, storage, T, n, A;
-    int i0, slot0, cnt, which;
-    size_t stride_act, stride_lp;    // bytes between slots
-    int act_bytes;                   // categorical: bytes of an action index in the plane (4 or 1)
-};
-void launch_cache_logp(const LogpArgs &a, hipStream_t s);
 
 }  // namespace impact
