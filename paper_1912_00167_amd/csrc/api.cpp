@@ -461,11 +461,14 @@ impact_status_t impact_buffer_gather(impact_buffer_t *buf, int32_t B, const int3
     const char *base = buf->storage;
     const int es = buf->es();
     (void)hipGetLastError();
+    GatherArgs a;
+    a.slots = dev_slots;
+    a.T = d.T;
+    a.B = B;
+    a.num_slots = d.num_slots;
+    a.num = 0;
     auto go = [&](size_t plane, size_t stride_bytes, const void *out, int Wd, int eb) {
-        if (!out) return;
-        GatherArgs a{base + plane, const_cast<void *>(out), dev_slots, d.T, B, Wd, d.num_slots, eb,
-                     stride_bytes / (size_t)eb};
-        launch_gather_plane(a, s);
+        if (out) a.task[a.num++] = GatherTask{base + plane, const_cast<void *>(out), stride_bytes, Wd, eb, 0, 0, 0};
     };
     const Planes &pl = buf->planes;
     if (pl.has_worker) go(pl.worker, pl.stride_dist, dst->worker_dist, buf->W(), es);
@@ -475,6 +478,7 @@ impact_status_t impact_buffer_gather(impact_buffer_t *buf, int32_t B, const int3
     else go(pl.actions, pl.stride_act, dst->actions, d.A, es);
     go(pl.rewards, pl.stride_rew, dst->rewards, 1, es);
     go(pl.dones, pl.stride_done, dst->dones, 1, 1);
+    launch_gather_plane(a, s);
     return hipGetLastError() == hipSuccess ? IMPACT_OK : IMPACT_ERR_HIP;
 }
 

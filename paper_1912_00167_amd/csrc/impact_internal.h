@@ -164,13 +164,23 @@ struct PlaneCopyArgs {
 enum PlaneKind { PLANE_F32, PLANE_BF16 };                  // what the ring stores the float fields as
 void launch_insert_plane(PlaneKind kind, const PlaneCopyArgs &a, hipStream_t s);
 
-struct GatherArgs {
-    const void *src;     // slot-major plane [N][T][Wd], slots slot_stride elements apart
+// ... and out of it: all fields of B slots in one launch.
+struct GatherTask {
+    const void *src;     // slot-major plane [N][T][Wd], slots slot_stride bytes apart
     void *dst;           // time-major [T][B][Wd]
-    const int32_t *slots;
-    int T, B, Wd, num_slots;
-    int elem_bytes;      // 1, 2 or 4
     size_t slot_stride;
+    int Wd;
+    int elem_bytes;      // 1, 2 or 4
+    int word_bytes;      // records: the largest of 4, 2, 1 that divides a record
+    int rows;            // records: time steps per tile; -1: scalars, by tile; 0: element by element
+    int end;             // first workgroup after this task's
+};
+constexpr int GATHER_TASKS = 6;
+struct GatherArgs {
+    const int32_t *slots;
+    int T, B, num_slots;
+    int num;
+    GatherTask task[GATHER_TASKS];
 };
 void launch_gather_plane(const GatherArgs &a, hipStream_t s);
 
