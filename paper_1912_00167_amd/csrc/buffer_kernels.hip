@@ -140,9 +140,22 @@ __device__ __forceinline__ void insert_elements(const PlaneCopyArgs &a, const Pl
     }
 }
 
-// log pi(a) of the action as the ring stores it, in fp64 with the library's exp and log, four lanes per step: this runs
-// once per trajectory, and is a chain of exponentials long (with one lane per step, 6.6 us for 128 trajectories of 50 steps,
-// A = 18, which was the longest launch of that insert).
+// Lane q of every four adjacent ones.
+template <int Q>
+__device__ __forceinline__ double of_quad(double x) { return dpp<Q * 0x55 /* quad_perm Q,Q,Q,Q */>(x); }
+// acc + the four lanes' terms in the order of the lanes
+__device__ __forceinline__ double add_quad(double acc, double x)
+{
+    acc += of_quad<0>(x);
+    acc += of_quad<1>(x);
+    acc += of_quad<2>(x);
+    return acc + of_quad<3>(x);
+}
+
+// log pi(a) of the action as the ring stores it, in fp64 with the library's exp and log: this runs once per trajectory, and
+// is a chain of exponentials long (with one lane per step, 6.6 us for 128 trajectories of 50 steps, A = 18, which was the
+// longest launch of that insert).  Four lanes share a step's exponentials; the sum goes through them in the order of the
+// elements, so that the stored bits do not depend on the split.
 template <typename ST>
 __device__ __forceinline__ void insert_logp(const PlaneCopyArgs &a, const PlaneTask &k, int block)
 {
@@ -165,22 +178,22 @@ __device__ __forceinline__ void insert_logp(const PlaneCopyArgs &a, const PlaneT
         m = fmaxf(m, dpp<DPP_XOR1>(m));
         m = fmaxf(m, dpp<DPP_XOR2>(m));
         double S = 0.0;
-        for (int c = part; c < l.A; c += 4) S += exp((double)z[c] - (double)m);
-        S += dpp<DPP_XOR1>(S);
-        S += dpp<DPP_XOR2>(S);
+        for (int c = 0; c < l.A; c += 4) {
+            const double x = exp((double)z[min(c + part, l.A - 1)] - (double)m);
+            S = add_quad(S, c + part < l.A ? x : 0.0);
+        }
         lp = ((double)z[act] - (double)m) - log(S);
     } else {
-        lp = 0.0;
-        for (int d = part; d < l.A; d += 4) {
+        lp = -l.A * (double)kHalfLog2Pi;
+        for (int c = 0; c < l.A; c += 4) {
+            const int d = min(c + part, l.A - 1);
             const double ls = (double)z[l.A + d];
             const double x = l.stride_act ? (double)widen(((const ST *)actions)[act_at * l.A + d])
                                           : (double)widen(convert<float, ST>(((const float *)actions)[act_at * l.A + d]));
             const double diff = x - (double)z[d];
-            lp += -0.5 * diff * diff * exp(-2.0 * ls) - ls;
+            const double term = -0.5 * diff * diff * exp(-2.0 * ls) - ls;
+            lp = add_quad(lp, c + part < l.A ? term : 0.0);
         }
-        lp += dpp<DPP_XOR1>(lp);
-        lp += dpp<DPP_XOR2>(lp);
-        lp -= l.A * (double)kHalfLog2Pi;
     }
     if (part == 0) ((double *)((char *)k.dst + (size_t)(a.slot0 + s) * k.slot_stride))[2 * t + k.which] = lp;
 }

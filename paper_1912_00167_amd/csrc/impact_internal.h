@@ -60,7 +60,6 @@ struct LossArgs {
     float4 *step_out;         // [T][B] records {dL/dV, vs, adv, 0} in place of the three tensors above, or null
     float *partials;          // [num_partials][PARTIAL_STRIDE]
     mutable int num_partials; // sets of partial sums the launch leaves (one per workgroup); set by the launcher
-    mutable bool dpp;         // the order in which their last sum combines (see reduce_tiles); set by the launcher
     // Long trajectories of a small batch are cut into num_segs time segments of seg_chunks chunks each,
     // one workgroup per (tile, segment).  The scan is affine in its carry, acc_t = A_t + P_t * carry, so a
     // first launch (phase 1) only finds every segment's A and P at its first step (seg_agg[seg][b][2]) and a
@@ -73,6 +72,7 @@ struct LossArgs {
     unsigned *done_count;
     float *loss5;
     float *fractions;         // [2] {clipped, truncated} shares of the steps, or null
+    mutable bool dpp;         // the order in which the partial sums' last sum combines (see reduce_tiles); set by the launcher
 };
 
 struct ReduceArgs {
