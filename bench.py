@@ -35,8 +35,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, AMD's published peak
 # is tied to the kernel sources it was taken on (kernel_sources_digest below): once any of them changes, the
 # benchmark reports null until the counters are taken again.
 MEASURED_TRAFFIC = {       # workload -> (bytes per launch, digest of the kernel sources at that time)
-    "C5": (2.0 * 344974 * 1024 + 311038 * 1024, "b97e71b7737558d7"),     # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
-    "C4": (2.0 * 97567 * 1024 + 69744 * 1024, "b97e71b7737558d7"),
+    "C5": (2.0 * 346104 * 1024 + 311482 * 1024, "ad9a0f12c995d63a"),     # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
+    "C4": (2.0 * 97692 * 1024 + 69755 * 1024, "ad9a0f12c995d63a"),
 }
 
 
